@@ -133,7 +133,10 @@ constexpr int CW = 8;          // waves per work-group of the code products
 // 8 codes (piece h of a word) as bf16.  2 bits: a nibble 00qq read as fp4 (e2m1) is q / 2, so a
 // conversion with scale 2 unpacks a byte, two codes, exactly; the nibbles of (word >> 2 b) &
 // 0x33333333, b = 0, 1, hold codes b, b + 2, b + 4, ...  (0.7 instructions a code; table
-// lookups with v_perm take 1.4.)  4 bits: bytes to float, whose upper halves are exact bf16.
+// lookups with v_perm take 1.4.)  4 bits: a byte 0000qqqq read as fp8 (e4m3) is q 2^-9 (its
+// subnormals and its first binade have one spacing), so a conversion with scale 512 unpacks two
+// codes exactly, one instruction a code.  (By way of v_cvt_f32_ubyte and v_perm, two: one token,
+// 9008 x 31536, whole call 95 us; 75 us so, 73 us on the vector unit.)
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 template <int BITS>
 __device__ __forceinline__ uint4 codes_bf16(uint32_t w, int h) {
@@ -149,12 +152,8 @@ __device__ __forceinline__ uint4 codes_bf16(uint32_t w, int h) {
 #pragma unroll
     for (int b = 0; b < 2; ++b) {
       const uint32_t y = (w >> (4 * b)) & 0x0F0F0F0Fu;
-#pragma unroll
-      for (int u = 0; u < 2; ++u) {
-        const uint32_t f0 = __float_as_uint((float)((y >> (16 * u)) & 0xFFu));
-        const uint32_t f1 = __float_as_uint((float)((y >> (16 * u + 8)) & 0xFFu));
-        q[2 * b + u] = __builtin_amdgcn_perm(f1, f0, 0x07060302u);
-      }
+      q[2 * b] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(y, 512.0f, 0));
+      q[2 * b + 1] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(y, 512.0f, 1));
     }
     o = make_uint4(q[0], q[1], q[2], q[3]);
   }
@@ -484,6 +483,16 @@ int apply_ksplit(int64_t d_in) {
   return (int)ks;
 }
 
+// Row tiles (16 rows, `ones` of the last one not code rows) per work-group: 3 share U's pieces, 2
+// for a single tile of U, whose pieces are few (12112 x 4512: 1 token 10.2 us with 2, 11.0 with 3,
+// 12.4 with 1; 80 tokens 72 with 2, 64 with 3, 66 with 4, event timer included), unless 3 need
+// one work-group a compute unit where 2 need a short second one (1 token, 4 bits, whole call:
+// 9008 x 31536 75 us with 2, 66 with 3; 12112 x 4512, 258 of them with 3: 29 and 30).
+int row_tiles(int ntiles, int64_t K_out, int ones) {
+  constexpr int64_t UNITS = 256;
+  return ntiles == 1 && (K_out <= UNITS * (32 - ones) || K_out > UNITS * (48 - ones)) ? 2 : 3;
+}
+
 template <int NT>
 hipError_t apply_block(const void* X, int xt, int64_t ldx, int nt, int64_t d_in,
                        const uint32_t* codes, int bits, const float* scale, const float* zero,
@@ -537,10 +546,7 @@ hipError_t apply_codes(const uint16_t* Uf, int nt, int bits, const uint32_t* cod
   const int cpw = 32 / bits;
   const int64_t nwords = (K_in + cpw - 1) / cpw, quads = codes_quads(K_in, bits);
   const int ntiles = (nt + CODES_TOK_F - 1) / CODES_TOK_F;
-  // row tiles per work-group: 3 share U's pieces, 2 for a single tile of U, whose pieces are
-  // few (12112 x 4512: 1 token 10.2 us with 2, 11.0 with 3, 12.4 with 1; 80 tokens 72 with 2,
-  // 64 with 3, 66 with 4, event timer included)
-  const int rt = ntiles == 1 ? 2 : 3, rows = 16 * rt - 1;
+  const int rt = row_tiles(ntiles, K_out, 1), rows = 16 * rt - 1;
   const dim3 g((unsigned)((K_out + rows - 1) / rows), (unsigned)ntiles);
   prof_begin(s, "apply_codes");
 #define FQ_CODES(B, R)                                                                           \
@@ -580,7 +586,7 @@ hipError_t apply_codes_i8(const int8_t* Cq, const float* delta, const int* csum,
   const int cpw = 32 / bits;
   const int64_t nwords = (K_in + cpw - 1) / cpw, quads = codes_quads(K_in, bits);
   const int ntiles = (nt + CODES_TOK_I - 1) / CODES_TOK_I;
-  const int rt = ntiles == 1 ? 2 : 3;                  // as in apply_codes
+  const int rt = row_tiles(ntiles, K_out, 0);
   const dim3 g((unsigned)((K_out + 16 * rt - 1) / (16 * rt)), (unsigned)ntiles);
   prof_begin(s, "apply_codes");
 #define FQ_CODES_I8(B, R)                                                                        \

@@ -65,3 +65,32 @@ def test_code_product_special_values(bits):
     Y = fq.fq_frame_apply(X, w, one, torch.zeros_like(ze), Po, Pi, bits=bits)
     q = torch.round(D / sc.double()[:, None] + ze.double()[:, None])
     assert torch.equal(Y.double(), (X.double() @ q.t().contiguous()).float().double())
+
+
+@pytest.mark.parametrize("bits", [2, 4])
+@pytest.mark.parametrize("K_out", [7936, 7952, 8192, 8208, 12032, 12048, 12288, 12304])
+def test_row_tiles_of_one_token_tile(bits, K_out):
+    """Row counts at which a single token tile takes 2 or 3 row tiles a work-group (31, 32, 47 and
+    48 times 256 rows): 5 tokens, one tile of float columns, as in 6, two tiles, and as in 64 bits."""
+    torch = need_gpu()
+    import paper_2403_06082_amd as fq
+    from test_gpu_tff_block import _frame
+    K_in = 16 * 9
+    w, sc, ze, _, Pi, D = _layer(torch, K_out, K_in, bits, K_out)
+    g = torch.Generator(device="cuda").manual_seed(K_out)
+    Po = torch.randn((8, K_out), generator=g, device="cuda") / np.sqrt(K_out)
+    X = torch.randn((6, K_in), generator=g, device="cuda")
+    Y = fq.fq_frame_apply(X, w, sc, ze, Po, Pi, bits=bits)
+    assert torch.equal(fq.fq_frame_apply(X[:5], w, sc, ze, Po, Pi, bits=bits), Y[:5])
+    ref = (X.double() @ D.t().contiguous()) @ Po.double().t().contiguous()
+    assert ((Y.double() - ref).norm() / ref.norm()).item() < 2e-6
+    # rounded activations: 16 tokens a tile
+    Fo, Pod = _frame(torch, fq, 96, K_out // 16, 16, 8, 1)
+    Fi, _ = _frame(torch, fq, 128, 9, 16, 8, 2)
+    X = torch.randn((17, 128), generator=g, device="cuda")
+    Y = fq.fq_frame_apply_tff_actq(X, w, sc, ze, Fo, Fi, 8, bits=bits)
+    assert torch.equal(fq.fq_frame_apply_tff_actq(X[:16], w, sc, ze, Fo, Fi, 8, bits=bits), Y[:16])
+    U = fq.fq_tff_analysis(X, Fi)
+    C, delta = fq.fq_act_quantize(U, 8)
+    ref = (C.double() * delta.double()[:, None]) @ D.t().contiguous() @ torch.from_numpy(Pod).cuda().t().contiguous()
+    assert ((Y.double() - ref).norm() / ref.norm()).item() < 2e-6
