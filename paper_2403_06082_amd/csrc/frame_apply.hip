@@ -19,12 +19,6 @@ namespace {
 
 constexpr int AT = 256;        // threads per work-group in every kernel here
 
-// Work-group barrier for LDS traffic only: waits for this wave's LDS operations, not for
-// its global loads (a fenced __syncthreads would also drain every load in flight).
-__device__ __forceinline__ void lds_barrier() {
-  asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-}
-
 template <typename T>
 __device__ __forceinline__ float to_f32(T v);
 template <>
