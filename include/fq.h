@@ -263,7 +263,8 @@ size_t fq_frame_apply_workspace_bytes(int64_t d_in, int64_t K_out, int64_t K_in)
  * R1 M R2^T.  Supported: d and rho even, d divisible by rho (the base frame's rows are
  * then blocks of m = d / rho ones), m <= k <= 3968, d1 d2 = d, d2 <= 4096.  R1, R2: device fp32,
  * row-major, owned by the caller.  The transforms below cost d (d1 + d2) + 2 d k FMAs per
- * vector and read no d x K matrix.
+ * vector and read no d x K matrix.  A vector's (token's) result, here and in the layer outputs
+ * below, is the same bits whatever other vectors share the call.
  */
 typedef struct fq_tff {
   int64_t d, k, rho;

@@ -130,11 +130,10 @@ struct TffDev {
 constexpr int64_t TFF_MAX_K = 3968;       // twiddles + one block of a vector within 64 KB of LDS
 constexpr int64_t TFF_MAX_D2 = 4096;     // one row of the rotation's d1 x d2 view in LDS
 constexpr int64_t TFF_CHUNK = 256;        // vectors per pass of the stand-alone transforms
-// U = X P for n vectors of a call of `total` (which alone picks the kernels); y: n x d scratch.
+// U = X P for n vectors; y: n x d scratch.  A vector's result does not depend on the others.
 // code_bits 0: U is n x (k rho) fp32; 2 or 4: U is stored for the product with codes of that
 // width (codes_layout.h).
-hipError_t tff_analysis(const void* X, int xt, int64_t ldx, int64_t n, int64_t total,
-                        const TffDev& F, float* y, void* U, int code_bits, hipStream_t s);
+hipError_t tff_analysis(const void* X, int xt, int64_t ldx, int64_t n, const TffDev& F, float* y, void* U, int code_bits, hipStream_t s);
 // P (d x k rho, row stride ldp) of the frame; Z, Pt: nc_max x d scratch each (one after the
 // other in memory), R2t: d2 x d2 scratch
 hipError_t tff_materialize(const TffDev& F, float* R2t, float* Z, float* Pt, int64_t nc_max,
@@ -183,11 +182,10 @@ bool is_side_stream(hipStream_t s);
 constexpr int64_t TFF_SEED_MAX_N = 1024;
 hipError_t tff_seeded_factors(uint64_t seed, int n0, int n1, double* G, double* V, double* ab,
                               float* out0, float* out1, hipStream_t s);
-// Y (n x ldy) = V P^T with V n x (k rho), n vectors of a call of `total`; block_order: V's
+// Y (n x ldy) = V P^T with V n x (k rho); block_order: V's
 // columns are [block c][subspace s][re, im] instead of the frame's s rho + 2c + e.  z: n x d
 // scratch, R2t: d2 x d2 scratch
-hipError_t tff_synthesis(const float* V, bool block_order, int64_t n, int64_t total,
-                         const TffDev& F, float* R2t, float* z, float* Y, int64_t ldy,
+hipError_t tff_synthesis(const float* V, bool block_order, int64_t n, const TffDev& F, float* R2t, float* z, float* Y, int64_t ldy,
                          hipStream_t s);
 
 // Per-token rounding of U (n x ldu, K columns) to act_bits-bit integers: Cq (code_bits 0: n x K

@@ -1,6 +1,6 @@
 """The structured transforms and layer outputs over token counts and frame shapes at which
-their launch forms change: the rotation fused with the block DFT or on its own, 1, 2, 4 or 8
-vectors a work-group, one or several token blocks, long rows of the rotation's view."""
+their launch forms change: rotations by rows or by 16-row tiles, DFTs of 1, 2, 4 or 8 vectors a
+work-group, one or several token blocks, long rows of the rotation's view."""
 import numpy as np
 import pytest
 
@@ -34,7 +34,7 @@ SHAPES = [
     (96, 13, 8, 8),          # d2 = 12: many thread groups a column
     (400, 55, 8, 16),        # d2 = 25, odd
     (1200, 80, 16, 2),       # d2 = 600 > 512 threads, rows of one block a part of a view row
-    (520, 70, 8, 260),       # d1 = 260: the left factor staged in three pieces, d2 = 2
+    (520, 70, 8, 260),       # d1 = 260 > 128, d2 = 2: view rows much shorter than a tile
     (2112, 150, 16, 33),     # d2 = 64, odd d1
 ]
 
@@ -59,6 +59,52 @@ def test_transforms_every_launch_form(d, k, rho, d1, n):
     back = U.double() @ Pd.t().contiguous()
     tol = 2.0 ** -24 * (8.0 + 2.0 * np.sqrt(d1 + d // d1 + k))
     assert ((Y.double() - back).norm() / back.norm()).item() < tol
+
+
+@pytest.mark.parametrize("d,k,rho,d1", SHAPES + [
+    (768, 53, 16, 24), (4096, 282, 16, 64), (11008, 757, 16, 86),
+    (2016, 139, 16, 2),      # d2 = 1008, the longest view row of the tiles
+    (2080, 143, 16, 2),      # d2 = 1040: rows at any count
+    (64, 17, 4, 1), (64, 17, 4, 64),
+    (16400, 1128, 16, 8200), # the left factor's rows read from memory
+])
+@pytest.mark.parametrize("scale", [1.0, 2.0 ** -124])      # results in the subnormal range too
+def test_a_vector_alone_and_in_a_batch(d, k, rho, d1, scale):
+    """A vector's transform is the same bits whatever other vectors share its call."""
+    torch = need_gpu()
+    import paper_2403_06082_amd as fq
+    g = torch.Generator(device="cuda").manual_seed(d)
+    F = fq.Frame(d, k, rho, *(torch.randn((n, n), generator=g, device="cuda") / np.sqrt(n) for n in (d1, d // d1)))
+    for dtype in (torch.float32, torch.float16, torch.bfloat16):
+        X = (torch.randn((20, d), generator=g, device="cuda") * (scale if dtype != torch.float16 else 1.0)).to(dtype)
+        V = torch.randn((20, F.K), generator=g, device="cuda") * scale
+        U, Y = fq.fq_tff_analysis(X, F), fq.fq_tff_synthesis(V, F)
+        for n in (1, 2, 7, 8, 17):
+            assert torch.equal(fq.fq_tff_analysis(X[:n], F), U[:n]), n
+            assert torch.equal(fq.fq_tff_synthesis(V[:n], F), Y[:n]), n
+        assert torch.equal(fq.fq_tff_analysis(X[19:], F), U[19:])
+        assert torch.equal(fq.fq_tff_synthesis(V[19:], F), Y[19:])
+
+
+@pytest.mark.parametrize("bits", [2, 4])
+def test_a_token_alone_and_in_a_batch(bits):
+    """Layer outputs too, with float and with rounded activations (where one bit can move a
+    rounded value)."""
+    torch = need_gpu()
+    import paper_2403_06082_amd as fq
+    g = torch.Generator(device="cuda").manual_seed(bits)
+    mk = lambda d, k, d1: fq.Frame(d, k, 16, *(torch.randn((n, n), generator=g, device="cuda") / np.sqrt(n)
+                                               for n in (d1, d // d1)))
+    Fo, Fi = mk(768, 53, 24), mk(1104, 76, 24)
+    words = torch.randint(-2 ** 31, 2 ** 31 - 1, (Fo.K, fq.fq.words_per_row(Fi.K, bits)), generator=g,
+                          device="cuda").to(torch.int32)
+    sc, ze = torch.rand(Fo.K, generator=g, device="cuda"), torch.full((Fo.K,), 1.0, device="cuda")
+    X = torch.randn((90, 1104), generator=g, device="cuda").bfloat16()
+    for f in (lambda x: fq.fq_frame_apply_tff(x, words, sc, ze, Fo, Fi, bits=bits),
+              lambda x: fq.fq_frame_apply_tff_actq(x, words, sc, ze, Fo, Fi, 8, bits=bits)):
+        Y = f(X)
+        for n in (1, 5, 6, 7, 8, 16, 17, 80):
+            assert torch.equal(f(X[:n]), Y[:n]), n
 
 
 @pytest.mark.parametrize("bits", [2, 4])
