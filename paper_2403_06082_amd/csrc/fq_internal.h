@@ -19,6 +19,20 @@ void prof_end(hipStream_t s);
 bool prof_enabled();
 hipError_t last_launch_error();
 
+// Launches a kernel whose dynamic LDS may go beyond 64 KB: the kernel's limit, which each device
+// keeps for itself, is then raised on the current device before every launch (a host call without
+// a stream), so that no state says on which devices it was.  Returns its error before launching.
+template <typename... P, typename... A>
+hipError_t launch_lds(void (*kernel)(P...), dim3 grid, dim3 block, size_t lds, hipStream_t s, A... args) {
+  if (lds > 64 * 1024) {
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return e;
+  }
+  hipLaunchKernelGGL(kernel, grid, block, (unsigned)lds, s, static_cast<P>(args)...);
+  return hipSuccess;
+}
+
 // ---------------------------------------------------------------- bf16 MFMA GEMM engine
 // C = sum over passes p of A[pa[p]] * B[pb[p]], fp32 accumulation, where A is M x K and
 // B is K x N, both given as 16-bit planes (bf16, or f16 for the Hessian of f16 inputs).

@@ -519,13 +519,6 @@ int dft_slices(int64_t nout, int64_t nb, int64_t groups) {
   return (int)std::max<int64_t>(1, std::min<int64_t>(want, (nout + WT / 64 - 1) / (WT / 64)));
 }
 
-// dynamic LDS beyond 64 KB needs the kernel's limit raised (once per instantiation)
-template <typename K>
-hipError_t allow_lds(K kernel) {
-  return hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
-                             hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-}
-
 size_t rot_lds(int d1, int d2) {
   if (rot_chains(d2) == 1) return (size_t)d2 * sizeof(float);
   return (size_t)(rot_pad(d2) + RC * d2 + (d1 <= ROT_ROW_D1 ? rot_pad(d1) : 0)) * sizeof(float);
@@ -666,7 +659,8 @@ __global__ __launch_bounds__(TT) void k_frame_rows(const float* __restrict__ R1,
 
 }  // namespace
 
-hipError_t tff_analysis(const void* X, int xt, int64_t ldx, int64_t n, const TffDev& F, float* y, void* U, int code_bits, hipStream_t s) {
+hipError_t tff_analysis(const void* X, int xt, int64_t ldx, int64_t n, const TffDev& F, float* y,
+                        void* U, int code_bits, hipStream_t s) {
   if (n == 0) return hipSuccess;
   hipError_t e;
   if (xt == 0) e = rotate_rows<float, true>((const float*)X, ldx, n, F, F.R2, y, F.d, s);
@@ -683,20 +677,18 @@ hipError_t tff_analysis(const void* X, int xt, int64_t ldx, int64_t n, const Tff
   const int64_t quads = code_bits > 0 ? codes_quads(F.k * F.rho, code_bits) : 0;
   const int ncol = codes_ncol_f(n);
 #define FQ_ANA(T, B)                                                                            \
-  { static const hipError_t attr = allow_lds(k_tff_analysis<T, B>); (void)attr;                  \
-    hipLaunchKernelGGL((k_tff_analysis<T, B>), g, dim3(WT), lds, s, y, F.d, (int)n, (int)F.k, (int)F.rho, \
-                       (int)F.m, scale, U, quads, ncol); }
+  e = launch_lds(k_tff_analysis<T, B>, g, dim3(WT), lds, s, y, F.d, n, F.k, F.rho, F.m, scale, U, quads, ncol);
 #define FQ_ANA_T(B) \
-  { if (T == 1) FQ_ANA(1, B) else if (T == 2) FQ_ANA(2, B) else if (T == 4) FQ_ANA(4, B) else FQ_ANA(8, B) }
+  { if (T == 1) { FQ_ANA(1, B) } else if (T == 2) { FQ_ANA(2, B) } else if (T == 4) { FQ_ANA(4, B) } else { FQ_ANA(8, B) } }
   if (code_bits == 0) FQ_ANA_T(0) else if (code_bits == 2) FQ_ANA_T(2) else FQ_ANA_T(4)
 #undef FQ_ANA_T
 #undef FQ_ANA
   prof_end(s);
-  return last_launch_error();
+  return e != hipSuccess ? e : last_launch_error();
 }
 
-hipError_t tff_synthesis(const float* V, bool block_order, int64_t n, const TffDev& F, float* R2t, float* z, float* Y, int64_t ldy,
-                         hipStream_t s) {
+hipError_t tff_synthesis(const float* V, bool block_order, int64_t n, const TffDev& F, float* R2t,
+                         float* z, float* Y, int64_t ldy, hipStream_t s) {
   if (n == 0) return hipSuccess;
   const int64_t nb = F.rho / 2;
   const int T = dft_vectors(n, F.k, F.k);
@@ -708,14 +700,15 @@ hipError_t tff_synthesis(const float* V, bool block_order, int64_t n, const TffD
   const float scale = (float)(1.0 / std::sqrt((double)F.k));
   const int64_t ldv = F.k * nb, ss = block_order ? 1 : nb, cs = block_order ? F.k : 1;   // complex
   prof_begin(s, "tff_dft");
+  hipError_t e = hipSuccess;
 #define FQ_SYN(T)                                                                               \
-  { static const hipError_t attr = allow_lds(k_tff_synthesis<T>); (void)attr;                    \
-    hipLaunchKernelGGL(k_tff_synthesis<T>, dim3((unsigned)(nwork + tb * tb)), dim3(WT), lds, s, \
-                       reinterpret_cast<const float2*>(V), ldv, ss, cs, (int)n, slices, (int)nwork, (int)F.k, (int)F.rho, (int)F.m, F.d, scale, z, \
-                       F.R2, F.d2, R2t); }
-  if (T == 1) FQ_SYN(1) else if (T == 2) FQ_SYN(2) else if (T == 4) FQ_SYN(4) else FQ_SYN(8)
+  e = launch_lds(k_tff_synthesis<T>, dim3((unsigned)(nwork + tb * tb)), dim3(WT), lds, s,       \
+                 reinterpret_cast<const float2*>(V), ldv, ss, cs, n, slices, nwork, F.k, F.rho, F.m, F.d, scale, z, \
+                 F.R2, F.d2, R2t);
+  if (T == 1) { FQ_SYN(1) } else if (T == 2) { FQ_SYN(2) } else if (T == 4) { FQ_SYN(4) } else { FQ_SYN(8) }
 #undef FQ_SYN
   prof_end(s);
+  if (e != hipSuccess) return e;
   return rotate_rows<float, false>(z, F.d, n, F, R2t, Y, ldy, s);
 }
 

@@ -713,7 +713,7 @@ __global__ __launch_bounds__(64 * NW) void k_rot_fused(const XT* __restrict__ X,
 }
 
 template <typename XT, bool SYN, int OUT>
-void launch_rot_fused(const XT* X, int64_t ldx, int64_t n, const TffDev& F, const RotOut& o,
+hipError_t launch_rot_fused(const XT* X, int64_t ldx, int64_t n, const TffDev& F, const RotOut& o,
                       hipStream_t s) {
   const int MT = fr_mt(F.d1), NW = fr_waves(F.d2);
   const int njb = (F.d2 + 16 * NW - 1) / (16 * NW);
@@ -746,19 +746,15 @@ void launch_rot_fused(const XT* X, int64_t ldx, int64_t n, const TffDev& F, cons
     vout = (F.d2 % 8 == 0 && o.bw % 8 == 0 && o.pb % 4 == 0 && o.ldp % 4 == 0 &&
             (reinterpret_cast<uintptr_t>(o.hi) & 7) == 0 &&
             (reinterpret_cast<uintptr_t>(o.lo) & 7) == 0);
-  // dynamic LDS beyond 64 KB needs the kernel's limit raised (once per instantiation)
-#define FR_LAUNCH(m, q, nw, kc) { \
-      static const hipError_t attr = hipFuncSetAttribute( \
-          reinterpret_cast<const void*>(k_rot_fused<XT, SYN, OUT, m, q, nw, kc>), \
-          hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024); \
-      (void)attr; \
-      hipLaunchKernelGGL((k_rot_fused<XT, SYN, OUT, m, q, nw, kc>), g, b, lds, s, X, ldx, n, F.R1, F.R2, F.d1, F.d2, vout, nv, o); }
+  hipError_t e = hipErrorInvalidValue;
+#define FR_LAUNCH(m, q, nw, kc) \
+      e = launch_lds(k_rot_fused<XT, SYN, OUT, m, q, nw, kc>, g, b, lds, s, X, ldx, n, F.R1, F.R2, F.d1, F.d2, vout, nv, o);
 #define FR_CASE(m) case m: \
-      if (fr_kc(F.d2) == 8) { if (small) FR_LAUNCH(m, 4, 8, 8) else FR_LAUNCH(m, 8, 8, 8) } \
-      else if (NW == 2) { if (small) FR_LAUNCH(m, 4, 2, 2) else FR_LAUNCH(m, 8, 2, 2) } \
-      else if (fr_kc(F.d2)) { if (small) FR_LAUNCH(m, 4, 4, 4) else FR_LAUNCH(m, 8, 4, 4) } \
-      else if (NW == 4) { if (small) FR_LAUNCH(m, 4, 4, 0) else FR_LAUNCH(m, FR_MAXQ, 4, 0) } \
-      else { if (small) FR_LAUNCH(m, 4, 8, 0) else FR_LAUNCH(m, 8, 8, 0) } \
+      if (fr_kc(F.d2) == 8) { if (small) { FR_LAUNCH(m, 4, 8, 8) } else { FR_LAUNCH(m, 8, 8, 8) } } \
+      else if (NW == 2) { if (small) { FR_LAUNCH(m, 4, 2, 2) } else { FR_LAUNCH(m, 8, 2, 2) } } \
+      else if (fr_kc(F.d2)) { if (small) { FR_LAUNCH(m, 4, 4, 4) } else { FR_LAUNCH(m, 8, 4, 4) } } \
+      else if (NW == 4) { if (small) { FR_LAUNCH(m, 4, 4, 0) } else { FR_LAUNCH(m, FR_MAXQ, 4, 0) } } \
+      else { if (small) { FR_LAUNCH(m, 4, 8, 0) } else { FR_LAUNCH(m, 8, 8, 0) } } \
       break;
   switch (MT) {
     FR_CASE(1) FR_CASE(2) FR_CASE(3) FR_CASE(4) FR_CASE(6) FR_CASE(8)
@@ -766,6 +762,7 @@ void launch_rot_fused(const XT* X, int64_t ldx, int64_t n, const TffDev& F, cons
   }
 #undef FR_CASE
 #undef FR_LAUNCH
+  return e;
 }
 
 // the fused kernel applies when d1 <= 128, d2 % 4 == 0, rows are aligned for 4-element
@@ -801,20 +798,21 @@ hipError_t rotate_rows(const void* X, int xt, int64_t ldx, int64_t n, const TffD
   const int vs2 = (F.d2 % 4 == 0 && al(F.R2, 16)) ? 1 : 0;
   const int vs1 = (F.d1 % 4 == 0 && al(F.R1, 16)) ? 1 : 0;
   prof_begin(s, name);
+  hipError_t e = hipSuccess;
   // the pass analyses into the block layout and synthesises into fp32 rows
   if (rot_fused_ok(F, X, esz, ldx) && synth == (OUT == 0)) {
     if constexpr (OUT == 0) {
-      launch_rot_fused<float, true, 0>((const float*)X, ldx, n, F, o, s);
+      e = launch_rot_fused<float, true, 0>((const float*)X, ldx, n, F, o, s);
     } else {
       if (xt == 0)
-        launch_rot_fused<float, false, OUT>((const float*)X, ldx, n, F, o, s);
+        e = launch_rot_fused<float, false, OUT>((const float*)X, ldx, n, F, o, s);
       else if (xt == 1)
-        launch_rot_fused<_Float16, false, OUT>((const _Float16*)X, ldx, n, F, o, s);
+        e = launch_rot_fused<_Float16, false, OUT>((const _Float16*)X, ldx, n, F, o, s);
       else
-        launch_rot_fused<uint16_t, false, OUT>((const uint16_t*)X, ldx, n, F, o, s);
+        e = launch_rot_fused<uint16_t, false, OUT>((const uint16_t*)X, ldx, n, F, o, s);
     }
     prof_end(s);
-    return last_launch_error();
+    return e != hipSuccess ? e : last_launch_error();
   }
   if (synth) {
     hipLaunchKernelGGL((k_rot_step<float, true, true, 0>), g, b, 0, s, (const float*)X, ldx, n, F.R2, F.d1, F.d2, vx, vs2, ot);

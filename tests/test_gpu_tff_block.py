@@ -147,3 +147,52 @@ def test_layer_outputs_token_blocks(bits, n):
         ys.append(fq.fq_frame_apply_tff_actq(X, words, sc, ze, Fo, Fi, 8, ws=ws, bits=bits))
     assert torch.equal(ys[0], ys[1])
     assert ((ys[0].double() - ref).norm() / ref.norm()).item() < 2e-2
+
+
+@pytest.mark.parametrize("d,k,rho,d1,n", [
+    (13824, 950, 16, 108, 17),    # 8 vectors of 950 subspaces a work-group: 68 KB of LDS
+    (6016, 1639, 4, 64, 3),       # 4 of 1639: 66 KB
+    (4000, 2457, 2, 50, 5),       # the most 4 take, 96 KB
+    (4000, 2458, 2, 50, 5),       # 2 from here on
+    (1456, 1365, 2, 26, 17),      # the most 8 take, 96 KB
+    (1456, 1366, 2, 26, 17),      # 4 from here on
+])
+def test_transforms_beyond_64_kb_of_lds(d, k, rho, d1, n):
+    """Synthesis and analysis against 64 bits where the vectors of a work-group need a raised LDS
+    limit, and where fewer vectors are taken, also replayed from a graph."""
+    torch = need_gpu()
+    import paper_2403_06082_amd as fq
+    g = torch.Generator(device="cuda").manual_seed(k)
+    R1, R2 = (torch.linalg.qr(torch.randn((s, s), generator=g, device="cuda", dtype=torch.float64))[0].float().contiguous()
+              for s in (d1, d // d1))
+    F = fq.Frame(d, k, rho, R1, R2)
+    X = torch.randn((n, d), generator=g, device="cuda")
+    V = torch.randn((n, F.K), generator=g, device="cuda")
+    m, nb = d // rho, rho // 2
+    ph = (torch.arange(d // 2, device="cuda")[:, None] * torch.arange(k, device="cuda")[None, :]) % k
+    E = torch.polar(torch.full(ph.shape, k ** -0.5, dtype=torch.float64, device="cuda"), ph.double() * (-2.0 * np.pi / k))
+    z = R1.double().t().contiguous() @ X.double().reshape(n, d1, d // d1) @ R2.double()
+    z = torch.view_as_complex(z.reshape(n, d // 2, 2).contiguous())
+    U = torch.stack([z[:, c * m:(c + 1) * m].contiguous() @ E[c * m:(c + 1) * m] for c in range(nb)], 2)
+    U = torch.view_as_real(U.contiguous()).reshape(n, F.K)
+    v = torch.view_as_complex(V.double().reshape(n, k, nb, 2).contiguous())
+    y = torch.cat([v[:, :, c].contiguous() @ E[c * m:(c + 1) * m].conj().t().resolve_conj().contiguous() for c in range(nb)], 1)
+    Y = torch.view_as_real(y.contiguous()).reshape(n, d1, d // d1)
+    Y = (R1.double() @ Y @ R2.double().t().contiguous()).reshape(n, d)
+    ws = torch.full((max(fq.fq_tff_analysis_workspace_bytes(n, F), fq.fq_tff_synthesis_workspace_bytes(n, F)),), 0xFF,
+                    dtype=torch.uint8, device="cuda")
+    u, o = torch.empty((n, F.K), device="cuda"), torch.empty((n, d), device="cuda")
+    graph, s = torch.cuda.CUDAGraph(), torch.cuda.Stream()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph, stream=s):
+        fq.fq_tff_analysis(X, F, u, ws=ws)
+        fq.fq_tff_synthesis(V, F, o, ws=ws)
+    for _ in range(3):
+        u.fill_(0.0), o.fill_(0.0), ws.fill_(0xFF)
+        graph.replay()
+        torch.cuda.synchronize()
+        # fp32 factors and twiddles and fp32 sums of d1 + d2 + m (k) terms, as above
+        tol = lambda terms: 2.0 ** -24 * (8.0 + 2.0 * np.sqrt(d1 + d // d1 + terms))
+        assert ((u.double() - U).norm() / U.norm()).item() < tol(m)
+        assert ((o.double() - Y).norm() / Y.norm()).item() < tol(k)
+    assert torch.equal(fq.fq_tff_analysis(X, F, ws=ws), u) and torch.equal(fq.fq_tff_synthesis(V, F, ws=ws), o)
