@@ -65,6 +65,10 @@ struct GemmDesc {
   u16* c_hi = nullptr;
   u16* c_lo = nullptr;
   int ksplit = 1;                // EPI_PARTIAL only
+  // EPI_PARTIAL of two M/N-major operands (asynchronous path): > 0 takes 128 x 128 tiles and folds
+  // their fp32 sums every `chain` K steps of 32 into a second set; a split then writes two
+  // partial slices, sums and remainders (2 ksplit in all)
+  int chain = 0;
   const char* name = "gemm";     // kernel-timer label
   int64_t ldc_pad = 0;           // EPI_SPLIT: output columns [N, ldc_pad) are zeroed
   // batch > 1 (EPI_F32, EPI_FOLD, EPI_PAIR): products z < batch read A + z bsa, B + z bsb and write
@@ -89,7 +93,7 @@ hipError_t gemm_run(const GemmDesc& d, float* partial, hipStream_t s);
 size_t gemm_tail_bytes();
 // whether gemm_run takes this product on the asynchronous path (any K-split of it)
 bool gemm_async_ok(const GemmDesc& d);
-// H (+)= sum of the ksplit partial tiles (fp64) + T^T T for ntail (at most 31) more rows T
+// H (+)= sum of the ksplit partial slices (fp64) + T^T T for ntail (at most 31) more rows T
 // (element type tt: 0 f32, 1 f16, 2 bf16; row stride ldt), mirrored to full symmetric storage.
 hipError_t syrk_reduce(const float* partial, int N, int ksplit, float* H, int64_t ldh,
                        int accumulate, const void* tail, int tt, int64_t ldt, int ntail,

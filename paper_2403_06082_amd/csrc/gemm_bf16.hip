@@ -21,6 +21,7 @@
 //    for L2 reuse.
 #include "fq_internal.h"
 
+#include <float.h>
 #include <stdlib.h>
 
 namespace fq {
@@ -462,6 +463,7 @@ struct AParams {
   int ra, rb;           // row extents the operand loads are clamped to (see gemm_run)
   int64_t bsa, bsb, bsc;  // element strides of A, B and C between the products of a batch
   int rowmap, fold_k, nvec;  // EPI_FOLD (see GemmDesc)
+  int chain;            // EPI_PARTIAL of 128-row tiles (see GemmDesc)
 };
 
 typedef __attribute__((address_space(3))) void lds_void;
@@ -557,16 +559,22 @@ __device__ __forceinline__ uint4 afrag(const char* base, const uint32_t (&f)[NB]
 // EPI_PAIR): 2 x 2 waves of 64 x 128 on a 128 x 256 tile with a ring of three stages
 // (72 KB), two work-groups per CU, so that one's stores overlap the other's product: a frame
 // block's products are short in K and store as much as they multiply (see gemm_run).
+// TBM = 128 with EPI_PARTIAL: 2 x 2 waves of 64 x 64 on a 128 x 128 tile, a ring of five stages
+// (80 KB), two work-groups per CU.  Half the accumulators leave room for a second set: every
+// p.chain stages the fp32 sums go into it and start anew from what that addition rounded away,
+// so that a split's sum loses no more than its chains of p.chain stages, however long it is.
 template <bool AMN, bool BMN, bool F16, int EPI, int TBM>
 __global__ __launch_bounds__(TBM * 2, TBM == 256 ? 1 : 2) void k_gemm_async(AParams p) {
   constexpr int WAVES = TBM / 32;
-  constexpr int ANST = TBM == 256 ? 5 : 3;       // ring stages
-  constexpr int NBM = TBM / 64;                  // 32-row blocks per wave in m
-  constexpr int NBN = TBM == 256 ? 2 : 4;        // 32-col blocks per wave in n
+  constexpr bool CHAIN = EPI == EPI_PARTIAL && TBM == 128;
+  constexpr int TBN = CHAIN ? 128 : BN;
+  constexpr int ANST = TBM == 256 || CHAIN ? 5 : 3;   // ring stages
   constexpr int WN = TBM == 256 ? 4 : 2;         // waves along n
+  constexpr int NBM = TBM / 64;                  // 32-row blocks per wave in m
+  constexpr int NBN = TBN / (32 * WN);           // 32-col blocks per wave in n
   // DMA chunks per lane and stage of A and B
-  constexpr int NIA = 4 * TBM / (64 * WAVES), NIB = 4 * BN / (64 * WAVES);
-  constexpr int ATILE = (TBM + BN) * ABK / 2;    // half a stage's u16 elements
+  constexpr int NIA = 4 * TBM / (64 * WAVES), NIB = 4 * TBN / (64 * WAVES);
+  constexpr int ATILE = (TBM + TBN) * ABK / 2;   // half a stage's u16 elements
   // one LDS object per ring stage, so that the compiler can tell the DMA writes of the
   // stages in flight from the reads of the stage being consumed
   __shared__ __attribute__((aligned(16))) u16 st0[2 * ATILE];
@@ -625,7 +633,7 @@ __global__ __launch_bounds__(TBM * 2, TBM == 256 ? 1 : 2) void k_gemm_async(APar
       tn = in / gs;
     }
   }
-  const int m0 = tm * TBM, n0 = tn * BN;
+  const int m0 = tm * TBM, n0 = tn * TBN;
   int kbeg = 0, kend = p.K;
   if (EPI == EPI_PARTIAL || EPI == EPI_TAIL) {
     kbeg = split * p.k_per_split;
@@ -636,18 +644,41 @@ __global__ __launch_bounds__(TBM * 2, TBM == 256 ? 1 : 2) void k_gemm_async(APar
 
   uint32_t ga[NIA], gb[NIB];
   dma_offsets<AMN, NIA, TBM>(p.lda, m0, p.ra, wave, lane, ga);
-  dma_offsets<BMN, NIB, BN>(p.ldb, n0, p.rb, wave, lane, gb);
+  dma_offsets<BMN, NIB, TBN>(p.ldb, n0, p.rb, wave, lane, gb);
   uint32_t fa[NBM][2], fb[NBN][2];
   frag_offsets<AMN, NBM, TBM>(wm * 32 * NBM, lane, fa);
-  frag_offsets<BMN, NBN, BN>(wn * 32 * NBN, lane, fb);
+  frag_offsets<BMN, NBN, TBN>(wn * 32 * NBN, lane, fb);
 
   floatx16 acc[NBM][NBN];
+  floatx16 sum[CHAIN ? NBM : 1][CHAIN ? NBN : 1];
 #pragma unroll
   for (int i = 0; i < NBM; ++i)
 #pragma unroll
     for (int j = 0; j < NBN; ++j)
 #pragma unroll
-      for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
+      for (int v = 0; v < 16; ++v) {
+        acc[i][j][v] = 0.f;
+        if (CHAIN) sum[i][j][v] = 0.f;
+      }
+  // sum + acc as (rounded sum, remainder): exact where |sum| >= |acc|, else off by at most one
+  // rounding of acc.  The remainder is kept finite, so that a sum that overflows stays infinite.
+  int left = p.chain;
+  auto end_stage = [&] {
+    if constexpr (CHAIN) {
+      if (--left > 0) return;
+      left = p.chain;
+#pragma unroll
+      for (int i = 0; i < NBM; ++i)
+#pragma unroll
+        for (int j = 0; j < NBN; ++j)
+#pragma unroll
+          for (int v = 0; v < 16; ++v) {
+            const float s = sum[i][j][v] + acc[i][j][v];
+            acc[i][j][v] = __builtin_amdgcn_fmed3f(acc[i][j][v] - (s - sum[i][j][v]), -FLT_MAX, FLT_MAX);
+            sum[i][j][v] = s;
+          }
+    }
+  };
 
   // Operand origins of each pass for this work-group's K range; inside a pass the stage
   // origin advances by a fixed byte step, so the issue path is pointer increments only.
@@ -694,7 +725,7 @@ __global__ __launch_bounds__(TBM * 2, TBM == 256 ? 1 : 2) void k_gemm_async(APar
 #pragma unroll
     for (int i = 0; i < NBM; ++i) af[i] = afrag<AMN, NBM, TBM>(sA, fa, i, kk);
 #pragma unroll
-    for (int j = 0; j < NBN; ++j) bf[j] = afrag<BMN, NBN, BN>(sB, fb, j, kk);
+    for (int j = 0; j < NBN; ++j) bf[j] = afrag<BMN, NBN, TBN>(sB, fb, j, kk);
   };
   auto mma = [&](const uint4 (&af)[NBM], const uint4 (&bf)[NBN]) {
 #pragma unroll
@@ -746,6 +777,7 @@ __global__ __launch_bounds__(TBM * 2, TBM == 256 ? 1 : 2) void k_gemm_async(APar
     }
     mma(a1, b1);
     interleave();
+    end_stage();
   };
 
   // steady-state step: stages up to s + ANST - 2 issued, stage s + ANST - 1 exists; straight-line
@@ -760,6 +792,7 @@ __global__ __launch_bounds__(TBM * 2, TBM == 256 ? 1 : 2) void k_gemm_async(APar
     load(nxt, 0, a0, b0);
     mma(a1, b1);
     interleave();
+    end_stage();
   };
 
   char* const r0 = reinterpret_cast<char*>(st0);
@@ -862,7 +895,15 @@ __global__ __launch_bounds__(TBM * 2, TBM == 256 ? 1 : 2) void k_gemm_async(APar
         const int cl = wn * 32 * NBN + j * 32 + (lane & 31);
         const int col = n0 + cl;
         const float x = acc[i][j][v];
-        if (EPI == EPI_PARTIAL) {
+        if (CHAIN) {
+          // its quarter of the 256 x 256 tile; slices 2 split (sums) and 2 split + 1 (remainders)
+          const int tm2 = tm >> 1, tn2 = tn >> 1, t2 = (p.tiles_n + 1) >> 1;
+          const int tidx = tm2 * t2 - (tm2 * (tm2 - 1)) / 2 + (tn2 - tm2);
+          float* dst = p.part + ((int64_t)(2 * split) * p.ntiles + tidx) * (BM * BN) +
+                       ((tm & 1) * 128 + rl) * BN + (tn & 1) * 128 + cl;
+          dst[0] = sum[i][j][v];
+          dst[(int64_t)p.ntiles * (BM * BN)] = x;
+        } else if (EPI == EPI_PARTIAL) {
           const int tidx = tm * p.tiles_n - (tm * (tm - 1)) / 2 + (tn - tm);
           p.part[((int64_t)split * p.ntiles + tidx) * (BM * BN) + rl * BN + cl] = x;
         } else if (EPI == EPI_TAIL) {
@@ -938,8 +979,8 @@ template <>
 __device__ __forceinline__ float ld_f<u16>(const u16* p) { return __uint_as_float((uint32_t)*p << 16); }
 
 // One work-group per (upper tile, SB x SB sub-block).  Sums the partial tiles in fp64, adds
-// the products of the ntail rows of T beyond the last whole K step (fp64, through LDS) and
-// the old H when accumulating, writes H[i][j] and (through LDS) H[j][i], i <= j.  Bound by
+// the products of the ntail rows of T beyond the last whole K step (through LDS, four products at
+// a time in fp32, those in fp64) and the old H when accumulating, writes H[i][j] and (through LDS) H[j][i], i <= j.  Bound by
 // reading the partial tiles; SB = 32 when 64 would leave the device half empty (few tiles).
 template <int SB, typename T>
 __global__ __launch_bounds__(256) void k_syrk_reduce(const float* __restrict__ part, int N,
@@ -950,8 +991,8 @@ __global__ __launch_bounds__(256) void k_syrk_reduce(const float* __restrict__ p
   constexpr int NS = BM / SB;                // sub-blocks per tile edge
   constexpr int TPR = SB / 4, RPP = 256 / TPR;   // threads per row, rows per pass
   __shared__ float tr[SB][SB + 1];
-  __shared__ __attribute__((aligned(16))) float ti[31][SB];
-  __shared__ __attribute__((aligned(16))) float tj[31][SB];
+  __shared__ __attribute__((aligned(16))) float ti[32][SB];
+  __shared__ __attribute__((aligned(16))) float tj[32][SB];
   const int sub = blockIdx.x % (NS * NS);
   const int tidx = blockIdx.x / (NS * NS);
   int t = tidx;
@@ -962,11 +1003,11 @@ __global__ __launch_bounds__(256) void k_syrk_reduce(const float* __restrict__ p
   const int i0 = tm * BM + sr * SB, j0 = tn * BN + sc * SB;
   if (i0 >= N || j0 >= N || i0 > j0) return;      // outside H, or below its diagonal
   if (ntail > 0) {
-    for (int e = threadIdx.x; e < ntail * SB; e += 256) {
+    for (int e = threadIdx.x; e < (ntail + 3) / 4 * 4 * SB; e += 256) {
       const int k = e / SB, c = e % SB;
       const T* row = tail + (int64_t)k * ldt;
-      ti[k][c] = i0 + c < N ? ld_f(row + i0 + c) : 0.f;
-      tj[k][c] = j0 + c < N ? ld_f(row + j0 + c) : 0.f;
+      ti[k][c] = k < ntail && i0 + c < N ? ld_f(row + i0 + c) : 0.f;
+      tj[k][c] = k < ntail && j0 + c < N ? ld_f(row + j0 + c) : 0.f;
     }
     __syncthreads();
   }
@@ -998,13 +1039,18 @@ __global__ __launch_bounds__(256) void k_syrk_reduce(const float* __restrict__ p
           sum[0] += v[q].x; sum[1] += v[q].y; sum[2] += v[q].z; sum[3] += v[q].w;
         }
     }
-    for (int k = 0; k < ntail; ++k) {
-      const double a = ti[k][r];
-      const float4 b = *reinterpret_cast<const float4*>(&tj[k][c4]);
-      sum[0] = fma(a, (double)b.x, sum[0]);
-      sum[1] = fma(a, (double)b.y, sum[1]);
-      sum[2] = fma(a, (double)b.z, sum[2]);
-      sum[3] = fma(a, (double)b.w, sum[3]);
+    for (int k = 0; k < ntail; k += 4) {
+      float f[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const float a = ti[k + q][r];
+        const float4 b = *reinterpret_cast<const float4*>(&tj[k + q][c4]);
+        f[0] = fmaf(a, b.x, f[0]);
+        f[1] = fmaf(a, b.y, f[1]);
+        f[2] = fmaf(a, b.z, f[2]);
+        f[3] = fmaf(a, b.w, f[3]);
+      }
+      sum[0] += f[0]; sum[1] += f[1]; sum[2] += f[2]; sum[3] += f[3];
     }
     const int i = i0 + r;
 #pragma unroll
@@ -1223,6 +1269,8 @@ hipError_t gemm_run(const GemmDesc& d, float* partial, hipStream_t s) {
   const bool fold = d.epi == EPI_FOLD || d.epi == EPI_PAIR;
   if (d.batch > 1 && ((d.epi != EPI_F32 && !fold) || d.batch > 65535 || d.bsa % 8 || d.bsb % 8))
     return hipErrorInvalidValue;
+  if (d.chain > 0 && (d.epi != EPI_PARTIAL || d.a_kmajor || d.b_kmajor || d.M != d.N || !gemm_async_ok(d)))
+    return hipErrorInvalidValue;
   // EPI_FOLD: A M-major and whole groups of 64 columns; EPI_PAIR: A K-major; both bf16, B K-major
   if (fold && (d.f16 || !d.b_kmajor || d.M % 2 || d.a_kmajor != (d.epi == EPI_PAIR) ||
                (d.epi == EPI_FOLD && d.N % 64)))
@@ -1262,7 +1310,7 @@ hipError_t gemm_run(const GemmDesc& d, float* partial, hipStream_t s) {
     q.ra = d.a_kmajor ? d.M : m8;
     q.rb = d.b_kmajor ? d.N : n8;
     q.bsa = d.bsa; q.bsb = d.bsb; q.bsc = d.bsc;
-    q.rowmap = d.rowmap; q.fold_k = d.fold_k; q.nvec = d.nvec;
+    q.rowmap = d.rowmap; q.fold_k = d.fold_k; q.nvec = d.nvec; q.chain = d.chain;
     const unsigned nbatch = (unsigned)d.batch;
     prof_begin(s, d.name);
 #define FQ_LAUNCH_ASYNC_E(AMN, BMN, F16, E, G)                                                        \
@@ -1308,7 +1356,15 @@ hipError_t gemm_run(const GemmDesc& d, float* partial, hipStream_t s) {
     const int tm128 = (d.M + 127) / 128;
     const int64_t t256 = (int64_t)p.ntiles * nbatch, t128 = (int64_t)tm128 * p.tiles_n * nbatch;
     const bool half = fold && (112 * t128 < 200 * t256 || t128 <= cus);
-    if (half) {
+    if (d.chain > 0) {             // EPI_PARTIAL of X^T X: both operands M/N-major
+      const int t128n = (d.N + 127) / 128;
+      q.tiles_m = q.tiles_n = t128n;
+      q.tile0 = 0;
+      q.tcount = t128n * (t128n + 1) / 2;
+      const dim3 cg((unsigned)(q.tcount * q.ksplit));
+      if (d.f16) hipLaunchKernelGGL((k_gemm_async<true, true, true, EPI_PARTIAL, 128>), cg, dim3(256), 0, s, q);
+      else hipLaunchKernelGGL((k_gemm_async<true, true, false, EPI_PARTIAL, 128>), cg, dim3(256), 0, s, q);
+    } else if (half) {
       q.tiles_m = tm128;
       q.ntiles = q.tcount = tm128 * p.tiles_n;
       q.tile0 = 0;

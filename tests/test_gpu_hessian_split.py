@@ -1,5 +1,6 @@
 """The Hessian's token split: whole K steps of 32 tokens in the asynchronous product, the
-rest with the reduction, and the number of splits chosen from the sizes."""
+rest with the reduction, splits and tiles chosen from the sizes, and fp32 sums that no choice
+makes longer."""
 import numpy as np
 import pytest
 
@@ -18,6 +19,10 @@ from fq_testutil import need_gpu
     (4099, 96, 96),       # one tile, many splits
     (65, 52, 52),         # extent not a multiple of 8
     (100, 40, 45),        # rows not 16-byte aligned: the register-staged product
+    (9000, 136, 136),     # two 128-column tiles, the second of 8 columns; many splits
+    (2500, 640, 640),     # five 128-column tiles: the last 256 x 256 tile has one quarter
+    (2600, 1160, 1160),
+    (600, 5768, 5768),    # two splits, 24 tokens left over: all in the register-staged product
 ])
 def test_token_remainders(dtype, n, d, ld):
     torch = need_gpu()
@@ -41,6 +46,57 @@ def test_token_remainders(dtype, n, d, ld):
     H0 = H.clone()
     fq.fq_hessian_accumulate(X, H, accumulate=True, ws=ws)
     assert ((H.double() - 2.0 * H0.double()).abs() <= 2.0 ** -22 * H0.double().abs()).all()
+
+
+def _longest_sum(n, d):
+    """Tokens of the longest fp32 sum: those of as many splits as the workspace holds."""
+    t = (d + 255) // 256
+    tiles, kt = t * (t + 1) // 2, (n + 63) // 64
+    splits = min(kt, max(1, (2048 + tiles // 2) // tiles))
+    return 64 * -(-kt // splits)
+
+
+@pytest.mark.parametrize("dtype,n,d", [("f16", 2037, 2048), ("bf16", 2048, 4096), ("bf16", 8192, 2048),
+                                       ("bf16", 25216, 768), ("bf16", 16384, 2048), ("f16", 40000, 256)])
+def test_error_of_the_fp32_sums(dtype, n, d):
+    """Off the diagonal (whose entries, all of one sign, are larger), against 64 bits, in units of
+    sqrt(H_ii H_jj), for Gaussian tokens.  Sums of L tokens in steps of 16, each rounded (c 2^-24
+    of the partial sum, c^2 = 1/3 on average), n / L of them added in fp64, and H rounded:
+    c 2^-24 sqrt((1 + L / 32) / n); c at most 0.85."""
+    torch = need_gpu()
+    import paper_2403_06082_amd as fq
+    dt = {"f16": torch.float16, "bf16": torch.bfloat16}[dtype]
+    code = {"f16": fq.FQ_F16, "bf16": fq.FQ_BF16}[dtype]
+    g = torch.Generator(device="cuda").manual_seed(n)
+    X = torch.randn((n, d), generator=g, device="cuda").to(dt)
+    H = torch.empty((d, d), device="cuda")
+    ws = torch.full((fq.fq_hessian_workspace_bytes(code, n, d),), 0xFF, dtype=torch.uint8, device="cuda")
+    fq.fq_hessian_accumulate(X, H, ws=ws)
+    ref = X.double().t().contiguous() @ X.double()
+    s = ref.diagonal().sqrt()
+    err = (((H.double() - ref) / (s[:, None] * s[None, :])).fill_diagonal_(0.0)).norm().item() / d
+    assert err < 0.85 * 2.0 ** -24 * np.sqrt((1.0 + _longest_sum(n, d) / 32.0) / n), err
+
+
+@pytest.mark.parametrize("n,d", [(2048, 2048), (2500, 640), (9000, 136), (65536, 256)])
+def test_overflow_and_special_values(n, d):
+    """A sum beyond fp32 is an infinity, a NaN or an infinity stays in its column and row."""
+    torch = need_gpu()
+    import paper_2403_06082_amd as fq
+    g = torch.Generator(device="cuda").manual_seed(d)
+    X = torch.randn((n, d), generator=g, device="cuda").bfloat16()
+    X[:, 3] = 1e19 * torch.sign(X[:, 3].float()).bfloat16()
+    X[n // 2, 70] = float("nan")
+    X[n // 3, 100] = float("inf")
+    H = torch.empty((d, d), device="cuda")
+    fq.fq_hessian_accumulate(X, H)
+    assert H[3, 3] == float("inf")
+    assert torch.isnan(H[70]).all() and torch.isnan(H[:, 70]).all()
+    assert (~torch.isfinite(H[100])).all() and H[100, 100] == float("inf")
+    ok = [j for j in range(d) if j not in (70, 100)]
+    rest = H[ok][:, ok].clone()
+    rest[3, 3] = 0.0
+    assert torch.isfinite(rest).all()
 
 
 def test_split_count_is_small_for_few_tiles():
