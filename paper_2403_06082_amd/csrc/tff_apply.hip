@@ -561,17 +561,23 @@ __device__ __forceinline__ float t_entry(float2 w, int e, int par) {
 }
 
 // G for columns c0 .. c0 + nc: G[(b na + r) ncp + col].  Lanes take columns; the products with
-// R2 are of a scalar and a per-lane entry.  grid (ceil(nc / 64), na, ceil(d2 / 64)), 4 waves
-// of 16 rows b each.  Dynamic LDS: k complex.
+// R2 are of a scalar and a per-lane entry, summed eight at a time (one sum of d2 = 64 terms: error
+// of P against 64 bits 1.8e-7 at d = 4096, 1.4e-7 when a work-group per row split it in 16).  The
+// twiddles carry the rounding of their angle as a correction.  grid (ceil(nc / 64), na,
+// ceil(d2 / 64)), 4 waves of 16 rows b each.  Dynamic LDS: k complex.
 constexpr int MB = 16;
+constexpr int GS = 8;       // terms per partial sum
 __global__ __launch_bounds__(TT) void k_frame_g(const float* __restrict__ R2, int d2, int k, int rho,
                                                 int m, float scale, int64_t c0, int64_t nc, int na,
                                                 int64_t ncp, float* __restrict__ G) {
   extern __shared__ __attribute__((aligned(16))) float sh[];
   float2* tws = reinterpret_cast<float2*>(sh);
   for (int t = threadIdx.x; t < k; t += TT) {
-    float sn, cs;
-    sincospif(2.0f * (float)t / (float)k, &sn, &cs);
+    const float x = 2.0f * (float)t / (float)k;
+    const float dx = fmaf(-x, (float)k, 2.0f * (float)t) / (float)k * 3.14159265f;   // radians
+    float s0, c0s;
+    sincospif(x, &s0, &c0s);
+    const float sn = fmaf(dx, c0s, s0), cs = fmaf(-dx, s0, c0s);
     tws[t] = make_float2(cs, sn);
   }
   __syncthreads();
@@ -586,9 +592,16 @@ __global__ __launch_bounds__(TT) void k_frame_g(const float* __restrict__ R2, in
   if (b0 >= d2) return;
   int p = (p0 / d2 + r) * d2;                          // coordinate of q = 0 in this view row
   int idx = (int)((uint32_t)((p >> 1) % k) * (uint32_t)s % (uint32_t)k);
-  float acc[MB];
+  float acc[MB], part[MB];
 #pragma unroll
-  for (int u = 0; u < MB; ++u) acc[u] = 0.f;
+  for (int u = 0; u < MB; ++u) acc[u] = part[u] = 0.f;
+  auto close = [&] {
+#pragma unroll
+    for (int u = 0; u < MB; ++u) {
+      acc[u] += part[u];
+      part[u] = 0.f;
+    }
+  };
   const float* rb[MB];
 #pragma unroll
   for (int u = 0; u < MB; ++u) rb[u] = R2 + (int64_t)min(b0 + u, d2 - 1) * d2;
@@ -598,21 +611,24 @@ __global__ __launch_bounds__(TT) void k_frame_g(const float* __restrict__ R2, in
       const bool in = p >= p0 && p < p1;
       const float t0 = in ? t_entry(t, e, 0) : 0.f, t1 = in ? t_entry(t, e, 1) : 0.f;
 #pragma unroll
-      for (int u = 0; u < MB; ++u) acc[u] = fmaf(rb[u][q + 1], t1, fmaf(rb[u][q], t0, acc[u]));
+      for (int u = 0; u < MB; ++u) part[u] = fmaf(rb[u][q + 1], t1, fmaf(rb[u][q], t0, part[u]));
       idx += s;
       if (idx >= k) idx -= k;
+      if (q % GS == GS - 2) close();
     }
   } else {
     for (int q = 0; q < d2; ++q, ++p) {
       const float t0 = (p >= p0 && p < p1) ? t_entry(tws[idx], e, p & 1) : 0.f;
 #pragma unroll
-      for (int u = 0; u < MB; ++u) acc[u] = fmaf(rb[u][q], t0, acc[u]);
+      for (int u = 0; u < MB; ++u) part[u] = fmaf(rb[u][q], t0, part[u]);
       if (p & 1) {
         idx += s;
         if (idx >= k) idx -= k;
       }
+      if (q % GS == GS - 1) close();
     }
   }
+  close();
   if (x >= nc) return;
 #pragma unroll
   for (int u = 0; u < MB; ++u)
@@ -725,7 +741,9 @@ hipError_t tff_materialize(const TffDev& F, float* R2t, float* Z, float* Pt, int
   const int64_t rows = frame_block_rows(F);
   // columns per pass: G takes na d2 floats of each, rounded up to 64 columns, in Z and Pt
   const int64_t fit = (Pt - Z) * 2 / (rows * F.d2) / 64 * 64;
-  if (rows <= 24 && fit >= 64) {
+  // (blocks over all rows of the view save nothing: 2080 = 2 x 1040 took 1028 us by blocks, 989
+  // by whole vectors, 3968 = 1 x 3968 14.4 and 13.2 ms)
+  if (rows <= 24 && rows < F.d1 && fit >= 64) {
     const int na = (int)rows;
     const bool lr = F.d1 <= 128;
     const size_t lds = lr ? (size_t)F.d1 * F.d1 * sizeof(float) : 0;
