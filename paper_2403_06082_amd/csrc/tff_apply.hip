@@ -741,9 +741,9 @@ hipError_t tff_materialize(const TffDev& F, float* R2t, float* Z, float* Pt, int
   const int64_t rows = frame_block_rows(F);
   // columns per pass: G takes na d2 floats of each, rounded up to 64 columns, in Z and Pt
   const int64_t fit = (Pt - Z) * 2 / (rows * F.d2) / 64 * 64;
-  // (blocks over all rows of the view save nothing: 2080 = 2 x 1040 took 1028 us by blocks, 989
-  // by whole vectors, 3968 = 1 x 3968 14.4 and 13.2 ms)
-  if (rows <= 24 && rows < F.d1 && fit >= 64) {
+  // (views of one or two rows are faster by whole vectors: 2080 = 2 x 1040 1017 us by blocks, 957
+  // so, 3968 = 1 x 3968 14.4 and 12.3 ms; 6000 = 3 x 2000 9.7 and 13.3)
+  if (rows <= 24 && F.d1 > 2 && fit >= 64) {
     const int na = (int)rows;
     const bool lr = F.d1 <= 128;
     const size_t lds = lr ? (size_t)F.d1 * F.d1 * sizeof(float) : 0;

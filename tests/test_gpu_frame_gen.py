@@ -18,7 +18,8 @@ pytestmark = pytest.mark.gpu
     (400, 27, 16, 16),     # blocks of 50 in rows of 25: 2 and 3 rows
     (2112, 150, 16, 132),  # d1 > 128: R1 read from memory; 17 or 18 rows a block
     (1536, 99, 16, 3),     # d2 = 512, a block within one or two rows, 1584 columns
-    (90, 19, 6, 2),        # blocks of 30 in rows of 45, all rows of the view: whole vectors
+    (90, 19, 6, 2),        # two view rows: whole vectors
+    (90, 19, 6, 3),        # blocks of 30 in rows of 30
     (4096, 257, 16, 64),   # 4112 columns
 ])
 def test_dense_frame_forms(d, k, rho, d1):
