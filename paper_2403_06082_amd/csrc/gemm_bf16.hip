@@ -979,9 +979,10 @@ template <>
 __device__ __forceinline__ float ld_f<u16>(const u16* p) { return __uint_as_float((uint32_t)*p << 16); }
 
 // One work-group per (upper tile, SB x SB sub-block).  Sums the partial tiles in fp64, adds
-// the products of the ntail rows of T beyond the last whole K step (through LDS, four products at
-// a time in fp32, those in fp64) and the old H when accumulating, writes H[i][j] and (through LDS) H[j][i], i <= j.  Bound by
-// reading the partial tiles; SB = 32 when 64 would leave the device half empty (few tiles).
+// the products of the ntail rows of T beyond the last whole K step (through LDS, four products
+// at a time in fp32, those sums in fp64) and the old H when accumulating, writes H[i][j] and
+// (through LDS) H[j][i], i <= j.  Bound by reading the partial tiles; SB = 32 when 64 would leave
+// the device half empty (few tiles).
 template <int SB, typename T>
 __global__ __launch_bounds__(256) void k_syrk_reduce(const float* __restrict__ part, int N,
                                                      int tiles, int ntiles, int ksplit,
