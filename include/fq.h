@@ -63,8 +63,9 @@ typedef enum { FQ_F32 = 0, FQ_F16 = 1, FQ_BF16 = 2 } fq_dtype;
  * H (+)= X^T X  -- the calibration Hessian (Sec. 3: the FF-space Hessian H~ = C C^T with
  * C = P_prev^T A_prev equals P_prev^T (X^T X) P_prev; A_prev = X^T).
  *   X        device, n_tokens x d_in, element type xt, row stride ldx >= d_in (elements).
- *            f16/bf16 products are exact in fp32; f32 X is split into two bf16 terms
- *            (relative error about 2^-17 per product).
+ *            f16/bf16 products are exact and summed in fp32 over at most as many tokens as
+ *            each of the workspace's partial sums would hold, those in fp64; f32 X is split
+ *            into two bf16 terms (relative error about 2^-17 per product).
  *   H        device fp32, d_in x d_in, row-major, written in full (exactly symmetric).
  *   accumulate  0: H = X^T X;  1: H += X^T X (chunked calibration sets).
  *   Cross-chunk sums are reduced in fp64 and rounded once to fp32.
@@ -237,7 +238,12 @@ size_t fq_frame_synthesis_workspace_bytes(int64_t K_out, int64_t K_in, int64_t d
  *   P_out  device fp32 d_out x K_out;  P_in device fp32 d_in x K_in.
  *   Y      device fp32, n_tokens x d_out, row-major (written; never read).
  *   ws     caller workspace of fq_frame_apply_workspace_bytes(d_in, K_out, K_in) bytes,
- *          16-byte aligned; its contents on entry do not matter.
+ *          16-byte aligned; its contents on entry do not matter.  That size holds a block of
+ *          8 tokens.  Where K_out < K_in, or K_out > S K_in with S the splits of d_in, a
+ *          smaller one is accepted too, down to the fp32 intermediates of 8 tokens,
+ *          4 (8 S K_in + 8 K_in + 8 K_out) bytes with each array rounded up; it holds at least
+ *          one token (5 as a rule) as the code product reads them, more go through in blocks,
+ *          each streaming the frames again, and the outputs do not depend on it.
  * Meant for decode and small batches: every frame and the codes are streamed once per
  * block of 8 tokens (for large token counts form Theta^ with fq_frame_synthesis and use a
  * GEMM).  fp32 arithmetic with fp32 accumulation.  n_tokens == 0 or d_out == 0 is a
@@ -300,9 +306,10 @@ size_t fq_tff_synthesis_workspace_bytes(int64_t n, const fq_tff* frame);
  * frame_in (d = d_in, K_in = k rho) and P_out is frame_out (d = d_out, K_out = k rho).
  * Reads no frame matrix.  X, codes, scale, zero, Y as in fq_frame_apply; ws:
  * fq_frame_apply_tff_workspace_bytes(frame_out, frame_in), which holds a block of 80 tokens
- * (more tokens go through in blocks).  A smaller workspace is accepted down to the 8-token
- * size 4 (8 (d_in + K_in + K_out + d_out) + d2_out^2) bytes, each array rounded up, and then
- * takes smaller blocks; the outputs do not depend on it.
+ * (more tokens go through in blocks).  A smaller workspace is accepted down to
+ * 4 (8 (d_in + K_in + K_out + d_out) + d2_out^2) bytes, each array rounded up, the fp32
+ * intermediates of 8 tokens, which hold at least one token as the code product reads them; it
+ * then takes smaller blocks, and the outputs do not depend on it.
  * Errors as fq_frame_apply and fq_tff_analysis.
  */
 fq_status fq_frame_apply_tff(void* stream, const void* X, int xt, int64_t n_tokens,
@@ -336,7 +343,7 @@ fq_status fq_frame_apply_tff_nbit(void* stream, const void* X, int xt, int64_t n
  * on one GPU share its array, so calls that overlap on
  * one GPU (different streams, or host threads without ordering) race and give undefined
  * outputs; order them on one stream.  Arguments, results and errors as
- * fq_frame_apply_tff_nbit; frames whose smallest workspace there exceeds
+ * fq_frame_apply_tff_nbit; frames whose smallest accepted workspace there exceeds
  * FQ_NOALLOC_SCRATCH_BYTES + 256 return FQ_ERR_UNSUPPORTED before any launch (16 MiB
  * covers frames with 8 (d_in + d_out + K_in + K_out) + d2_out^2 floats up to 4 Mi, e.g.
  * d_in = 28672, d_out = 8192, r = 1.1).  Tokens go through in blocks of as many as fit.

@@ -118,7 +118,7 @@ constexpr int APPLY_BLOCK = 80;
 struct ApplyScratch {
   float* part;   // split-K partials of U = X P_in
   uint16_t* Uf;  // U as the code product reads it (codes_layout.h)
-  float* V;      // tokens x K_out
+  float* V;      // tokens x K_out; as a rule in the place of part
   int nt;        // tokens per block
 };
 // floats of scratch for blocks of nt <= APPLY_NT tokens (and, with base, the carve-up); base

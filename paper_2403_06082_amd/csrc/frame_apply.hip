@@ -611,8 +611,9 @@ size_t apply_scratch_floats(int64_t d_in, int64_t K_out, int64_t K_in, int nt, A
   ApplyScratch l{};
   l.nt = nt;
   l.part = take((size_t)(ks_eff * rows * K_in));
-  l.Uf = reinterpret_cast<uint16_t*>(take((size_t)(codes_bytes_f(K_in, 2, nt) / 4 + 1)));
-  l.V = take((size_t)(rows * K_out));
+  l.Uf = reinterpret_cast<uint16_t*>(take((size_t)((codes_bytes_f(K_in, 2, nt) + 3) / 4)));
+  // V goes where the partials were, which are summed by then, unless it is larger
+  l.V = K_out <= ks_eff * K_in ? l.part : take((size_t)(rows * K_out));
   if (w) *w = l;
   return off;
 }

@@ -248,3 +248,18 @@ def test_frame_choice_matches_the_oracle(L):
     assert L.fq_tff_choose(22, 1.1, 8, ctypes.byref(k), None, None) == 2
     assert L.fq_tff_choose(255, 1.1, 16, ctypes.byref(k), None, None) == 1
     assert L.fq_tff_choose(256, -1.0, 16, ctypes.byref(k), None, None) == 1
+
+
+@pytest.mark.parametrize("d_in,K_out,K_in", [(4096, 12112, 4512), (768, 3376, 848), (4096, 4576, 4512), (11008, 12208, 12112)])
+def test_dense_apply_workspace_is_the_fp32_intermediates(L, d_in, K_out, K_in):
+    """Split partials, U and V of 8 tokens in fp32 hold a whole block of 8 where K_out >= K_in."""
+    ks = 64
+    while ks > 1 and d_in // ks < 32:
+        ks //= 2
+    if -(-d_in // ks) > 256:
+        ks = -(-d_in // 256)
+    ks = -(-d_in // -(-d_in // ks))
+    r64 = lambda n: -(-n // 64) * 64
+    L.fq_frame_apply_workspace_bytes.restype = ctypes.c_size_t
+    want = 4 * (r64(ks * 8 * K_in) + r64(8 * (-(-K_in // 16) * 16)) + r64(8 * K_out)) + 256
+    assert L.fq_frame_apply_workspace_bytes(ctypes.c_int64(d_in), ctypes.c_int64(K_out), ctypes.c_int64(K_in)) == want

@@ -111,7 +111,7 @@ def test_a_token_alone_and_in_a_batch(bits):
 @pytest.mark.parametrize("n", [1, 5, 6, 16, 17, 80, 81, 163])
 def test_layer_outputs_token_blocks(bits, n):
     """The same outputs, bit for bit, with any accepted workspace: the size the query states,
-    and the smallest accepted (8 tokens a block)."""
+    and the smallest accepted (blocks of fewer tokens)."""
     torch = need_gpu()
     import paper_2403_06082_amd as fq
     Fo, Po = _frame(torch, fq, 400, 27, 16, 16, 3)
