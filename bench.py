@@ -415,10 +415,10 @@ def structured_bench(fq, torch, dev, bufs, wl, li, K_out, K_in, tokens=(1, 8), i
             "per_tokens": rows,
             "int8_activations": {"op": "fq_frame_apply_tff_actq, act_bits 8: the analysis output "
                                        "rounded per token to int8, code products exact in int32 "
-                                       "(v_dot4)", "per_tokens": qrows},
+                                       "(v_mfma_i32_16x16x64_i8)", "per_tokens": qrows},
             "note": "about 7.6e7 FMAs per token (5.5e7 in the code GEMV) and 13.8 MB of codes "
-                    "per block of 8 tokens: bound by launch and memory latency at 1 token, by "
-                    "the code kernel's VALU work at 8"}
+                    "per block of up to 80 tokens: bound by five dependent launches of 4-8 us at 1 "
+                    "token, by those and the output frame's block DFT at 8"}
 
 
 def grid_variants_bench(torch, dev, wl, li, L, K_out, K_in, n, steps, iters=200, frames=None):
